@@ -110,12 +110,10 @@ struct DmaK {
 // (four per operand) measured 214 us, 146 us and 3 % slower elsewhere.
 // V j values per lane (V = min(d, 4)): STRIDED when d > V (pieces of V
 // elements at stride d), otherwise the lane's LP x V block is contiguous.
-// Register budget per instance: the smallest tiles (MT = NT = 1) are fitted
-// to four waves per SIMD (four workgroups per CU), NT = 2 to three, the rest
-// to two (the accumulators then live in VGPRs instead of AGPRs).
+// The body of the two kernels below, one with K operands straight into
+// registers, one with K operands through LDS.
 template <typename T, int V, bool STRIDED, int MT, int LP, int UD, int NT, bool KLDS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT * NT == 1 ? 4 : ((MT == 1 && NT == 2) ? 3 : 2))))
-void ks_dma_kernel(Problem p, StagedTile t) {
+__device__ __forceinline__ void dma_body(Problem p, StagedTile t) {
   constexpr int S = sizeof(T);
   constexpr int CH = 4 * LP;  // values of l per stage
   constexpr int PE = STRIDED ? V : (LP * V * S < 16 ? LP * V : 16 / S);
@@ -375,16 +373,34 @@ void ks_dma_kernel(Problem p, StagedTile t) {
   }
 }
 
+// Register budget per instance: the smallest tiles (MT = NT = 1) are fitted
+// to four waves per SIMD (four workgroups per CU), NT = 2 to three, the rest
+// to two (the accumulators then live in VGPRs instead of AGPRs).
+constexpr int dma_waves(int MT, int NT) { return MT * NT == 1 ? 4 : ((MT == 1 && NT == 2) ? 3 : 2); }
+template <typename T, int V, bool STRIDED, int MT, int LP, int UD, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dma_waves(MT, NT))))
+void ks_dma_kernel(Problem p, StagedTile t) {
+  dma_body<T, V, STRIDED, MT, LP, UD, NT, false>(p, t);
+}
+template <typename T, int V, bool STRIDED, int MT, int LP, int UD, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dma_waves(MT, NT))))
+void ks_dma_klds_kernel(Problem p, StagedTile t) {
+  dma_body<T, V, STRIDED, MT, LP, UD, NT, true>(p, t);
+}
+
 template <typename T, int V, bool STRIDED, int MT, int LP, int UD, int NT, bool KLDS>
 hipError_t launch_dma_inst(const Problem& p, const StagedTile& t, hipStream_t s) {
+  void (*kernel)(Problem, StagedTile);
+  if constexpr (KLDS) kernel = ks_dma_klds_kernel<T, V, STRIDED, MT, LP, UD, NT>;
+  else kernel = ks_dma_kernel<T, V, STRIDED, MT, LP, UD, NT>;
   if (t.lds > 64 * 1024) {
     // Opt in to more than 64 KB of dynamic LDS once per instance (a function-
     // local static: initialised exactly once even with concurrent callers).
-    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void*>(&ks_dma_kernel<T, V, STRIDED, MT, LP, UD, NT, KLDS>),
+    static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaMaxLds);
     if (raised != hipSuccess) return raised;
   }
-  hipLaunchKernelGGL((ks_dma_kernel<T, V, STRIDED, MT, LP, UD, NT, KLDS>), dim3(t.tiles), dim3(256), t.lds, s, p, t);
+  hipLaunchKernelGGL(kernel, dim3(t.tiles), dim3(256), t.lds, s, p, t);
   return hipGetLastError();
 }
 

@@ -305,9 +305,9 @@ std::string kernel_name(const Problem& p, const Plan& pl) {
       }
       // DMA instructions per wavefront per stage: 16*rs rows of lch*d*esize
       // bytes over four wavefronts of 64 16-byte lanes.
-      snprintf(buf, sizeof buf, "ks_dma_kernel<%s,%d,%s,%d,%d,%d,%d,%s>", t, pl.vec, pl.unroll ? "true" : "false",
-               pl.waves_m, pl.cps, (int)(pl.rs * pl.nt * pl.lch * p.d * (p.dtype == F32 ? 4 : 2) / 256), pl.nt,
-               pl.klds ? "true" : "false");
+      snprintf(buf, sizeof buf, "ks_dma_%skernel<%s,%d,%s,%d,%d,%d,%d>", pl.klds ? "klds_" : "", t, pl.vec,
+               pl.unroll ? "true" : "false", pl.waves_m, pl.cps,
+               (int)(pl.rs * pl.nt * pl.lch * p.d * (p.dtype == F32 ? 4 : 2) / 256), pl.nt);
       break;
     case V_MASKED:
       if (pl.unroll)

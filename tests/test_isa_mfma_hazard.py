@@ -80,7 +80,7 @@ def test_scanner_flags_a_read_at_the_minimum_distance():
 # Kernels whose arguments must arrive in one round of scalar loads (mangled
 # name fragments: length-prefixed identifiers).
 ONE_ROUND_FAMILIES = ("18ks_direct_c_kernel", "16ks_direct_kernel", "17ks_dma_bsl_kernel")
-BSF_DMA = "13ks_dma_kernel"
+BSF_DMA = ("13ks_dma_kernel", "18ks_dma_klds_kernel")
 
 
 def _argument_rounds(lines):
@@ -111,7 +111,7 @@ def test_kernel_arguments_arrive_in_one_round(kernel_asm):
                 checked += 1
                 if _argument_rounds(lines) > 1:
                     bad.append((f, fn))
-            elif BSF_DMA in fn:
+            elif any(k in fn for k in BSF_DMA):
                 dma += 1
                 r = _argument_rounds(lines)
                 dma_one += r == 1

@@ -233,3 +233,15 @@ def test_long_rows_keep_the_register_kernel():
     desc = ks.ks_plan_describe(1, 33, 33, 4096, 8, "bsf", "f32")
     assert "name=masked" in desc and "kernel=ks_masked_kernel<float,0," in desc, desc
     assert "kernel=ks_masked_bsf_kernel<" in ks.ks_plan_describe(1, 33, 33, 16, 8, "bsf", "f32")
+
+
+def test_dma_forms_have_their_own_names():
+    """Batch-size-first DMA: the name of the kernel with K operands in registers
+    has seven arguments, the one with K operands in LDS is another kernel."""
+    def kernel(*call):
+        return dict(f.split("=", 1) for f in ks.ks_plan_describe(*call).split())["kernel"]
+    assert kernel(2, 64, 64, 4, 4096, "bsf", "f32").startswith("ks_dma_kernel<float,4,false,")
+    for call in ((6, 64, 16, 8, 25088, "bsf", "bf16"), (1, 128, 128, 16, 25088, "bsf", "f32")):
+        name = kernel(*call)
+        assert name.startswith("ks_dma_klds_kernel<" if call[2] == 128 else "ks_dma_kernel<"), name
+        assert name.count(",") == 6
