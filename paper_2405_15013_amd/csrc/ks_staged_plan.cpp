@@ -227,28 +227,41 @@ struct DmaPrefs {
 // K through LDS (dma_k_slot) frees the address unit, which takes 64 cycles for
 // an operand loaded into registers and 16 for one moved by DMA, and costs 16
 // cycles of LDS traffic per operand and up to 32 KB of LDS.  It pays where K
-// loads fill the stages.  Timed on every feasible tile of 1400 batch-size-first
-// calls (batch 1024 to 25088, fp32 and bf16) against the best tile with K in
-// registers: d = 16 gains 9 % from c = 96 (fp32 also from b, c = 64), d = 8 from
-// c = 128 or, where b splits evenly over the k-groups (a multiple of 64), c = 96,
-// d = 4 from c = 128 unless four k-groups of one tile share X already.  In those
-// classes (one call in seven) the rule is 7 % faster in the mean, up to 1.46x,
-// ten calls lose 3-6 %; below c = 64 K in registers is 2 % faster, a stage's
-// latency being all that counts.
+// loads fill the stages.  Timed against K in registers on 2400 batch-size-first
+// calls (fp32 and bf16, b 16 to 256, c 64 to 256, a 1 to 8, batch 1024 to
+// 25088), on buffers that change from call to call, and on 340 of them on
+// buffers that stay.  Time with K in LDS over time with K in registers, mean
+// per (b, c) where it is used: fp32 d = 16 0.87-0.97, d = 8 0.85-0.96, d = 4
+// 0.86-0.98; 16-bit d = 16 0.70-0.95, d = 8 0.75-0.97, d = 4 0.78-0.95.  Single
+// calls lose up to 1.18 (33 of 2880 more than 5 %: fp32 with b = 96 or 192 and
+// few tiles, and b = 16 with d = 4 and long batches).  Where it
+// is not used: an odd number of stages with b small or not split evenly (fp32
+// c = 112, 144: 0.98-1.16; 16-bit c = 160: 0.96-1.11); 16-bit d = 16 with c = 96
+// (0.97-1.05); fp32 d = 8 with b = 32, 64, 96, 160, 192 and c = 96, 128 (0.97
+// to 1.15, on buffers that stay up to 1.23).  Below c = 64 K in registers is 2 %
+// faster, a stage's latency being all that counts.
 bool dma_k_through_lds(const Problem& p) {
-  const bool f32 = p.dtype == F32;
-  if (!f32 && p.c % 32) return false;  // 16x16x16 stages: operand rows of 32 bytes
+  const int b = p.b, c = p.c;
+  if (p.dtype == F32) {
+    switch (p.d) {
+      case 16: return (c >= 96 || (c >= 64 && b >= 64)) && (c % 32 == 0 || b > 64);
+      case 8: return c % 32 == 0 && (c >= 160 || (c >= 128 && b % 32 != 0) || (c >= 96 && b % 128 == 0));
+      case 4: return c % 32 == 0 && c >= 128 && b % 64 != 0;
+      default: return false;
+    }
+  }
+  if (c % 32) return false;  // 16x16x16 stages: operand rows of 32 bytes
   switch (p.d) {
-    case 16: return (p.c >= 96 && (f32 || p.c >= 128 || p.b % 32 == 0)) || (f32 && p.c >= 64 && p.b >= 64);
-    case 8: return p.c >= 128 || (p.c >= 96 && p.b % 64 == 0);
-    case 4: return p.c >= 128 && p.b % 64 != 0;
+    case 16: return c >= 128 && (c % 64 == 0 || b % 32 == 0);
+    case 8: return b % 64 == 0 ? c >= 96 : (c >= 128 && c % 64 == 0);
+    case 4: return c >= 128 && c % 64 == 0 && b % 64 != 0;
     default: return false;
   }
 }
 DmaPrefs dma_prefs(const Problem& p) {
   const bool f32 = p.dtype == F32;
   if (dma_k_through_lds(p)) return {f32 && p.d >= 16 && p.b >= 64 ? 128 * 1024 : 80 * 1024, f32 ? 4 : 2, true};
-  // fp32 with d = 16, b >= 64 and c = 48: the 64 KB preference would leave
+  // fp32 with d = 16, b >= 64 and c >= 48: the 64 KB preference would leave
   // 16-row tiles (four j-groups take the four wavefronts) whose stages hold too
   // few MFMAs to cover the next stage's K loads; 32-row tiles in up to 128 KB
   // measured 4-18 % faster (median per c) there, and slower with one or two

@@ -245,3 +245,17 @@ def test_dma_forms_have_their_own_names():
         name = kernel(*call)
         assert name.startswith("ks_dma_klds_kernel<" if call[2] == 128 else "ks_dma_kernel<"), name
         assert name.count(",") == 6
+
+
+@pytest.mark.parametrize("dtype,inside,outside", [
+    ("f32", [(1, 64, 64, 16), (1, 16, 96, 16), (1, 48, 128, 8), (2, 128, 96, 8), (1, 64, 160, 8), (1, 96, 128, 4)],
+     [(1, 48, 112, 16), (2, 64, 96, 8), (2, 64, 128, 8), (1, 192, 128, 8), (1, 48, 144, 8), (1, 64, 128, 4),
+      (1, 48, 144, 4)]),
+    ("bf16", [(1, 64, 128, 16), (1, 64, 160, 16), (1, 64, 96, 8), (1, 48, 128, 8), (1, 48, 192, 4)],
+     [(1, 32, 96, 16), (4, 128, 96, 16), (1, 48, 160, 16), (1, 48, 160, 8), (1, 48, 160, 4), (1, 64, 128, 4)])])
+def test_k_through_lds_only_where_it_pays(dtype, inside, outside):
+    """K operands move through LDS in the classes that measured faster, and stay
+    in registers in those that measured the same or slower."""
+    for pattern in inside + outside:
+        desc = ks.ks_plan_describe(*pattern, 4096, "bsf", dtype)
+        assert ("kernel=ks_dma_klds_kernel<" in desc) == (pattern in inside), desc
