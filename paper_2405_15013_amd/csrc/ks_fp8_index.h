@@ -29,7 +29,11 @@ constexpr int fp8_rows_waves(int mt, int nch, bool half) {
 // True when the call takes the long-row kernel: d = 8, whole 16-row tiles of b,
 // 16-byte pieces of X and Y, 8-byte K operands that fit the registers
 // (c <= 64).  All walks are equally long but for one tile, and are no more
-// than the chip holds at a time.
+// than the chip holds at a time.  Left to ks_fp8_kernel: calls of one batch tile
+// per walk with the most K operands (two tiles of b, c of 64), which a walk of
+// one tile does not earn back (34 calls of batch 1 to 4096: 1.02 of its time
+// in the mean, up to 1.13; c of 56 and less 0.76-0.98, longer walks 0.42-0.91).
+// d other than 8 and c above 64 have not been tried in this form.
 inline bool fp8_rows(const Problem& p, Fp8Rows* t) {
   if (p.dtype != FP8 || p.layout != BSF || p.d != 8 || p.b % 16 || p.c % 8 || p.c > 64 || p.align < 16) return false;
   if (reinterpret_cast<uintptr_t>(p.kv) % 8) return false;
@@ -41,6 +45,7 @@ inline bool fp8_rows(const Problem& p, Fp8Rows* t) {
   const int64_t resident = 256 * 4 * fp8_rows_waves(t->mt, nch, p.c - 32 * (nch - 1) <= 16);  // 256 CUs of 4 SIMDs
   const int64_t most = walks < resident ? resident / walks : 1;
   const int64_t tiles = (t->nbt + most - 1) / most;  // of a walk
+  if (tiles == 1 && t->mt == 2 && p.c > 56) return false;
   t->nseg = (int)((t->nbt + tiles - 1) / tiles);
   if (walks * t->nseg > 0x7fffffff - 3) return false;
   t->items = (int)(walks * t->nseg);

@@ -259,3 +259,14 @@ def test_k_through_lds_only_where_it_pays(dtype, inside, outside):
     for pattern in inside + outside:
         desc = ks.ks_plan_describe(*pattern, 4096, "bsf", dtype)
         assert ("kernel=ks_dma_klds_kernel<" in desc) == (pattern in inside), desc
+
+
+def test_fp8_long_rows_only_where_they_pay():
+    """FP8 walks of one batch tile with 64 values of l and two row tiles measured
+    slower than the general kernel, and keep it."""
+    for pattern, batch, rows in [((8, 96, 64, 8), 4, False), ((4, 64, 64, 8), 197, False), ((4, 64, 56, 8), 197, True),
+                                 ((4, 48, 64, 8), 197, True), ((4, 64, 64, 8), 25088, True)]:
+        desc = ks.ks_plan_describe(*pattern, batch, "bsf", "fp8")
+        assert ("kernel=ks_fp8_rows_kernel<" in desc) == rows, desc
+        st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", "fp8")
+        assert st == 0, rep
