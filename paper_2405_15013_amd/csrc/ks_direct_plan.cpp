@@ -142,7 +142,7 @@ bool plan_ragged_bsl(const Problem& p, Plan* pl) {
   while (V < vmax && 16 * V < p.batch) V *= 2;
   const int64_t groups = (int64_t)((p.batch + 16 * V - 1) / (16 * V)) * p.a * p.d;
   const int MT = ragged_mt(KT, V == 8 ? 2 : 4, 1024, [&](int kg) { return groups * kg; });
-  if (groups * ((KT + MT - 1) / MT) > 0x7fffffff - 3) return false;
+  if ((groups * ((KT + MT - 1) / MT) + 3) / 4 > kMaxGrid256) return false;
   const RaggedTile t = ragged_bsl_tile(p, V, MT);
   pl->variant = V_MASKED;
   pl->unroll = 1;
@@ -173,7 +173,7 @@ bool plan_ragged_bsf(const Problem& p, Plan* pl) {
       const RaggedTile t = ragged_bsf_tile(p, rg, 1, 16 * kt);
       if (t.lds > kRaggedMaxLds) continue;
       const int64_t wgs = (int64_t)t.nbt * p.a * t.kgroups;
-      if (wgs > 0x7fffffff) continue;
+      if (wgs > kMaxGrid256) continue;
       // enough workgroups, then room for two per CU, then fewer reads of K, then of X
       const int64_t score = ((wgs < 512 ? wgs : 512) << 20) + (t.lds <= kRaggedMaxLds / 2 ? 1 << 16 : 0) + (rg << 12) + kt;
       if (score > best_score) {
@@ -211,7 +211,7 @@ bool plan_masked(const Problem& p, Plan* pl) {
   const int V = masked_vec(p);
   const MaskedTile t = masked_tile(p, V);
   const int64_t items = (int64_t)t.nbt * p.a * t.jgroups * t.kgroups;
-  if (items > 0x7fffffff - 3) return false;
+  if ((items + 3) / 4 > kMaxGrid256) return false;
   pl->variant = V_MASKED;
   pl->vec = V;
   pl->unroll = 0;

@@ -91,4 +91,8 @@ inline int valu_bsl_unroll(int b, int c) {
   return m <= 2 ? 4 : (m <= 4 ? 2 : 1);
 }
 constexpr int kValuMaxBC = 16;
+
+// Most workgroups of 256 threads in one launch: the HIP runtime refuses a
+// launch of 2^32 threads and more.
+constexpr int64_t kMaxGrid256 = 0xffffffffll / 256;
 }  // namespace ks

@@ -270,3 +270,15 @@ def test_fp8_long_rows_only_where_they_pay():
         assert ("kernel=ks_fp8_rows_kernel<" in desc) == rows, desc
         st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", "fp8")
         assert st == 0, rep
+
+
+@pytest.mark.parametrize("pattern,batch,layout", [
+    ((17000000, 5, 1, 1), 1, "bsf"), ((15000000, 8, 16, 1), 4, "bsf"), ((17000000, 17, 1, 1), 1, "bsf"),
+    ((33000000, 33, 1, 1), 1, "bsf"), ((70000000, 5, 1, 1), 1, "bsl"), ((70000000, 17, 1, 1), 1, "bsl"),
+    ((1, 5, 5, 70000000), 2, "bsl"), ((1, 17, 1, 100000000), 1, "bsl"), ((1, 1, 33, 60000000), 1, "bsf")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_plans_of_many_blocks_can_be_launched(pattern, batch, layout, dtype):
+    """The runtime refuses 2^32 threads and more: a call of millions of blocks
+    gets a kernel whose launch stays below that."""
+    f = dict(x.split("=", 1) for x in ks.ks_plan_describe(*pattern, batch, layout, dtype).split())
+    assert int(f["grid"]) * int(f["block"]) < 1 << 32, f
