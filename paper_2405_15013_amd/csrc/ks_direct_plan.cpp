@@ -205,9 +205,10 @@ RaggedTile ragged_tile_of(const Problem& p, const Plan& pl) {
                          : ragged_bsf_tile(p, pl.vec, pl.waves_m, 16 * pl.kgw);
 }
 
-bool plan_masked(const Problem& p, Plan* pl) {
-  if (p.layout == BSL) return plan_ragged_bsl(p, pl);
-  if (plan_ragged_bsf(p, pl)) return true;
+// Batch-size-first, register kernel: one wavefront per (batch tile, j-group, 16
+// rows), however few batch rows there are.
+bool plan_masked_reg(const Problem& p, Plan* pl) {
+  if (p.layout != BSF) return false;
   const int V = masked_vec(p);
   const MaskedTile t = masked_tile(p, V);
   const int64_t items = (int64_t)t.nbt * p.a * t.jgroups * t.kgroups;
@@ -224,6 +225,41 @@ bool plan_masked(const Problem& p, Plan* pl) {
   pl->grid = (unsigned)((items + 3) / 4);
   pl->xcd_remap = 0;
   return true;
+}
+
+// Where rows through LDS are the faster batch-size-first form.  Its workgroup
+// takes the d * b / (16 MT) products of a tile one after the other on four
+// wavefronts, which the register kernel has a wavefront each for: with few
+// workgroups that chain is the call's time ((2,3,34,37) fp32 at batch 104 4.5 us
+// in registers, 13.5 us through LDS; (3,29,2,228) bf16 at batch 1 3.8, 41.9 us),
+// with many the shared X rows and whole-line stores win (down to 0.17 of the
+// register kernel's time).  Timed both ways on 878 calls with b or c above 16
+// (batch 1 to 30000, fp32 and bf16): below 16 batch rows the LDS form is slower
+// unless a wavefront has one product of a long sum; above, it pays from eight
+// workgroups per product of the chain, with at least 6 KB of rows to share.  Of
+// those calls this rule leaves 36 more than 5 % behind the register kernel alone
+// (without it 219) and the mean at 0.71 of its time.
+bool ragged_bsf_pays(const Problem& p, const Plan& pl) {
+  const int kgroups = (pl.kgw + pl.waves_m - 1) / pl.waves_m;
+  const int64_t chain = ((int64_t)kgroups * p.d + 3) / 4;  // products per wavefront
+  if (p.batch < 16) return chain == 1 && p.c >= 64;
+  return pl.grid >= 8 * chain && pl.lds_bytes >= 6000;
+}
+
+// The masked kernel when it is asked for: ks_ragged.h's wherever it can run.
+bool plan_masked(const Problem& p, Plan* pl) {
+  if (p.layout == BSL) return plan_ragged_bsl(p, pl);
+  return plan_ragged_bsf(p, pl) || plan_masked_reg(p, pl);
+}
+
+// The faster masked kernel.
+bool plan_masked_auto(const Problem& p, Plan* pl) {
+  if (p.layout == BSL) return plan_ragged_bsl(p, pl);
+  Plan lds;
+  const bool fits = plan_ragged_bsf(p, &lds);
+  if (!(fits && ragged_bsf_pays(p, lds)) && plan_masked_reg(p, pl)) return true;
+  if (fits) *pl = lds;
+  return fits;
 }
 
 hipError_t launch_masked(const Problem& p, const Plan& pl, hipStream_t s) {

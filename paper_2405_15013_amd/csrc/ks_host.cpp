@@ -115,6 +115,7 @@ bool plan_direct(const Problem& p, bool al16, Plan* pl);
 bool plan_staged(const Problem& p, bool al16, Plan* pl);
 bool plan_dma(const Problem& p, bool al16, Plan* pl);
 bool plan_masked(const Problem& p, Plan* pl);
+bool plan_masked_auto(const Problem& p, Plan* pl);
 bool plan_fp8(const Problem& p, Plan* pl);
 namespace {
 
@@ -162,10 +163,10 @@ bool plan_auto(const Problem& p, bool al16, Plan* pl) {
   // slower, batch-size-last 0.7-1.3; 2 x 2 blocks 1.1 to 3 times faster.
   const int m = p.b > p.c ? p.b : p.c;
   const bool small = m <= 2 || (m <= 4 && (p.layout == BSL || p.a * p.d < 64));
-  if (!small && plan_masked(p, pl)) return true;
+  if (!small && plan_masked_auto(p, pl)) return true;
   if (p.layout == BSL && plan_valu_bsl(p, al16, pl)) return true;
   if (p.layout == BSF && plan_valu_bsf(p, al16, pl)) return true;
-  if (plan_masked(p, pl)) return true;
+  if (plan_masked_auto(p, pl)) return true;
   return plan_generic(p, pl);
 }
 

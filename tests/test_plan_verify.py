@@ -232,7 +232,7 @@ def test_long_rows_keep_the_register_kernel():
     """Batch-size-first rows that do not fit LDS: the register kernel."""
     desc = ks.ks_plan_describe(1, 33, 33, 4096, 8, "bsf", "f32")
     assert "name=masked" in desc and "kernel=ks_masked_kernel<float,0," in desc, desc
-    assert "kernel=ks_masked_bsf_kernel<" in ks.ks_plan_describe(1, 33, 33, 16, 8, "bsf", "f32")
+    assert "kernel=ks_masked_bsf_kernel<" in ks.ks_plan_describe(1, 33, 33, 16, 4096, "bsf", "f32")
 
 
 def test_dma_forms_have_their_own_names():
@@ -282,3 +282,16 @@ def test_plans_of_many_blocks_can_be_launched(pattern, batch, layout, dtype):
     gets a kernel whose launch stays below that."""
     f = dict(x.split("=", 1) for x in ks.ks_plan_describe(*pattern, batch, layout, dtype).split())
     assert int(f["grid"]) * int(f["block"]) < 1 << 32, f
+
+
+@pytest.mark.parametrize("pattern,batch,dtype,lds", [
+    ((3, 29, 2, 228), 1, "bf16", False), ((2, 3, 34, 37), 104, "f32", False), ((1, 33, 33, 16), 8, "f32", False),
+    ((21, 33, 4, 9), 6, "bf16", False), ((1, 115, 28, 37), 26, "f32", False), ((2, 40, 130, 1), 4, "f32", True),
+    ((1, 33, 33, 16), 4096, "f32", True), ((6, 110, 80, 3), 5504, "bf16", True), ((4, 29, 89, 5), 3327, "bf16", True)])
+def test_masked_rows_through_lds_where_there_are_enough(pattern, batch, dtype, lds):
+    """Batch-size-first masked calls: rows through LDS only with the workgroups
+    to hide the chain of products of each; both forms replayed."""
+    desc = ks.ks_plan_describe(*pattern, batch, "bsf", dtype)
+    assert ("kernel=ks_masked_bsf_kernel<" if lds else "kernel=ks_masked_kernel<") in desc, desc
+    st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", dtype)
+    assert st == 0, rep
