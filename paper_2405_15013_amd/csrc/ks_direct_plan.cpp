@@ -252,6 +252,12 @@ bool plan_masked(const Problem& p, Plan* pl) {
   return plan_ragged_bsf(p, pl) || plan_masked_reg(p, pl);
 }
 
+// Batch-size-first: the faster masked kernel is the one with rows in LDS.
+bool masked_rows_in_lds(const Problem& p) {
+  Plan lds;
+  return plan_ragged_bsf(p, &lds) && ragged_bsf_pays(p, lds);
+}
+
 // The faster masked kernel.
 bool plan_masked_auto(const Problem& p, Plan* pl) {
   if (p.layout == BSL) return plan_ragged_bsl(p, pl);

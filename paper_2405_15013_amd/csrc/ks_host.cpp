@@ -116,6 +116,7 @@ bool plan_staged(const Problem& p, bool al16, Plan* pl);
 bool plan_dma(const Problem& p, bool al16, Plan* pl);
 bool plan_masked(const Problem& p, Plan* pl);
 bool plan_masked_auto(const Problem& p, Plan* pl);
+bool masked_rows_in_lds(const Problem& p);
 bool plan_fp8(const Problem& p, Plan* pl);
 namespace {
 
@@ -131,6 +132,35 @@ bool plan_variant(int v, const Problem& p, bool al16, Plan* pl) {
     case V_FP8: return plan_fp8(p, pl);
     default: return false;
   }
+}
+
+// Where the VALU kernels are the faster ones for blocks that the aligned MFMA
+// kernels do not take (b, c <= 16).  Their threads fetch a whole block each, so
+// their time grows with b * c, while the masked MFMA kernels pad the block to
+// 16 x 16; vectors of V j or of the batch let a thread's fetch serve V columns.
+// Timed both ways on 6000 calls (batch 1 to 25088, a 1 to 64, d 1 to 600, fp32,
+// bf16, f16; X + Y up to 200 MB), masked time over VALU time:
+//  * batch-size-first, b or c of 1: 1.0-1.1 in small calls, 1.5-2.9 from 2 MB of
+//    X + Y; b * c just below 32, 24, 16, 12 at V = 1, 2, 4, 8: 1.10, 1.14, 1.27,
+//    1.02 (above 2 MB; 0.4-0.9 in small ones, where both are near a launch);
+//    twice that b * c 0.55, 0.5, 0.41, 0.55.  Rows left to the register kernel
+//    (ks_masked.h), which gathers them, with d >= 100: half as much again.
+//    Of 3665 calls this leaves 42 more than 5 % behind the VALU kernel (with
+//    b, c > 4 alone as the line 441), the mean at 0.40 of its time.
+//  * batch-size-last: up to 4 x 4; and whole vectors of the batch with b * c
+//    below 32 from 4 MB of X + Y, where the VALU kernel is at the copy rate
+//    (1.0-1.8, single calls 2.7; 0.6-0.8 in smaller calls and odd batches).  Of
+//    2335 calls this leaves 14 more than 5 % behind, the mean at 0.51.
+bool valu_pays(const Problem& p, bool al16, int64_t xy_bytes) {
+  const int m = p.b > p.c ? p.b : p.c;
+  if (m > kValuMaxBC) return false;
+  const int bc = p.b * p.c, vec16 = 16 / elem_size(p.dtype);
+  if (p.layout == BSL) return m <= 4 || (al16 && p.batch % vec16 == 0 && bc < 32 && xy_bytes >= (4 << 20));
+  if (p.b == 1 || p.c == 1) return true;
+  int v = 1;
+  while (al16 && v < vec16 && p.d % (2 * v) == 0) v *= 2;
+  const int line = v == 1 ? 32 : (v == 2 ? 24 : (v == 4 ? 16 : 12));
+  return bc < line || (p.d >= 100 && 2 * bc < 3 * line && !masked_rows_in_lds(p));
 }
 
 // Automatic choice: MFMA block GEMM when b and c make each (i, j) block a real
@@ -156,14 +186,7 @@ bool plan_auto(const Problem& p, bool al16, Plan* pl) {
   const bool bsl_dma = p.dtype == F32 || ((p.b & (p.b - 1)) == 0 && p.b >= 32 && p.c <= 64);
   if (p.layout == BSL && bsl_dma && plan_dma(p, al16, pl)) return true;
   if (plan_direct(p, al16, pl)) return true;
-  // Small blocks.  The VALU kernels' threads fetch a whole block each, so
-  // their time grows with b * c while the masked MFMA kernels pad the block to
-  // 16 x 16 (batch 64 to 6815, fp32 and bf16): b or c above 4, VALU 1.1 to 15
-  // times slower in both layouts; (16,4,4,16) batch-size-first 1.3-2.9 times
-  // slower, batch-size-last 0.7-1.3; 2 x 2 blocks 1.1 to 3 times faster.
-  const int m = p.b > p.c ? p.b : p.c;
-  const bool small = m <= 2 || (m <= 4 && (p.layout == BSL || p.a * p.d < 64));
-  if (!small && plan_masked_auto(p, pl)) return true;
+  if (!valu_pays(p, al16, xy_bytes) && plan_masked_auto(p, pl)) return true;
   if (p.layout == BSL && plan_valu_bsl(p, al16, pl)) return true;
   if (p.layout == BSF && plan_valu_bsf(p, al16, pl)) return true;
   if (plan_masked_auto(p, pl)) return true;

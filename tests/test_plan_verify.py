@@ -295,3 +295,21 @@ def test_masked_rows_through_lds_where_there_are_enough(pattern, batch, dtype, l
     assert ("kernel=ks_masked_bsf_kernel<" if lds else "kernel=ks_masked_kernel<") in desc, desc
     st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", dtype)
     assert st == 0, rep
+
+
+@pytest.mark.parametrize("pattern,batch,layout,dtype,valu", [
+    ((2, 1, 15, 95), 2273, "bsf", "f32", True), ((4, 15, 1, 453), 429, "bsf", "f16", True),
+    ((2, 5, 3, 139), 2261, "bsf", "f16", True), ((2, 5, 3, 128), 2261, "bsf", "f16", False),
+    ((1, 4, 4, 256), 4096, "bsf", "f32", True), ((4, 4, 4, 512), 4096, "bsf", "f32", True),
+    ((16, 4, 4, 16), 4096, "bsf", "f32", False), ((1, 8, 8, 128), 4096, "bsf", "f32", False),
+    ((1, 8, 8, 256), 25088, "bsf", "bf16", False), ((2, 4, 4, 2), 32, "bsf", "f32", True),
+    ((16, 5, 1, 32), 18240, "bsl", "bf16", True), ((16, 5, 1, 32), 18241, "bsl", "bf16", False),
+    ((1, 5, 1, 32), 512, "bsl", "bf16", False), ((8, 4, 4, 16), 100, "bsl", "f32", True)])
+def test_small_blocks_run_the_faster_kernel(pattern, batch, layout, dtype, valu):
+    """b, c <= 16: the VALU kernels where their fetch of whole blocks is the
+    cheaper one, the masked MFMA kernels elsewhere."""
+    desc = ks.ks_plan_describe(*pattern, batch, layout, dtype)
+    assert ("kernel=ks_valu_%s_kernel<" % layout in desc) == valu, desc
+    assert valu or "name=masked" in desc, desc
+    st, rep = ks.ks_plan_verify(*pattern, batch, layout, dtype)
+    assert st == 0, rep
