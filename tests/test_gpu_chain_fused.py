@@ -145,8 +145,8 @@ def test_hadamard_chain_bit_exact_both_paths(layout, fused):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("layout", ["bsf", "bsl"])
-@pytest.mark.parametrize("b,q", [(16, 8), (16, 16), (16, 64), (32, 8), (32, 32), (32, 64), (48, 8), (48, 16), (64, 8),
-                                 (64, 16)])
+@pytest.mark.parametrize("b,q", [(16, 8), (16, 16), (16, 32), (16, 64), (32, 8), (32, 16), (32, 32), (32, 64), (48, 8),
+                                 (48, 16), (64, 8), (64, 16)])
 def test_pair_chain(b, q, layout, dtype):
     """The two-factor kernel on every instance's sizes: one column, a tile cut
     short, one tile per workgroup and several (batch-size-last: batches of
@@ -163,7 +163,13 @@ def test_pair_chain(b, q, layout, dtype):
         yd = nan_tensor((batch * N,), dtype)
         need = ks.ks_chain_workspace_bytes(factors, batch, dtype)
         ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+        desc = ks.ks_chain_describe(factors, batch, layout, dtype)
+        # instances: both factors' values and a tile of X in a workgroup's registers
+        runs = (b // 16) ** 2 * (q // 8)
+        pair = runs <= (18 if dtype == "f32" else 32) if layout == "bsf" else (
+            dtype != "f32" and runs <= 18 and batch % 4 == 0 and (N <= 256 or batch >= 64 * 191 + 1))
+        assert ("pair=1" in desc) == pair, (batch, desc)
         ks.ks_chain(factors, xd, yd, batch, layout, dtype, ws, need)
         torch.cuda.synchronize()
         y = inputs.from_layout(from_device(yd, dtype).reshape((batch, N) if layout == "bsf" else (N, batch)), layout)
-        assert rel_err(y, y64) <= TOL[dtype], (batch, ks.ks_chain_describe(factors, batch, layout, dtype))
+        assert rel_err(y, y64) <= TOL[dtype], (batch, desc)

@@ -414,6 +414,56 @@ def test_ragged_edges(pattern, layout, dtype, batch):
     check(pattern, batch, dtype, layout, cfg=23, variant=VARIANTS["masked"], x_offset=1, y_offset=1, kdist="normal")
 
 
+# Instances of the masked kernels: 1, 2 and 4 row tiles per wavefront, every
+# vector width (batch-size-last) and number of row groups (batch-size-first), b
+# off the tile, whole chunks of l and one cut short; the register kernel's
+# widths.  (pattern, batch, layout, kernel's numbers in fp32, in 16 bits)
+MASKED_INSTANCES = [
+    ((16, 61, 77, 32), 7, "bsl", "1,2", "1,2"), ((16, 109, 77, 32), 7, "bsl", "1,4", "1,4"),
+    ((16, 61, 77, 32), 31, "bsl", "2,2", "2,2"), ((16, 109, 77, 32), 31, "bsl", "2,4", "2,4"),
+    ((1, 29, 77, 3), 31, "bsl", "2,1", "2,1"), ((16, 61, 77, 32), 33, "bsl", "4,2", "4,2"),
+    ((16, 109, 77, 32), 33, "bsl", "4,4", "4,4"), ((1, 29, 77, 3), 33, "bsl", "4,1", "4,1"),
+    ((6, 77, 37, 5), 2051, "bsl", "4,2", "8,2"), ((1, 29, 77, 3), 130, "bsl", "4,1", "8,1"),
+    ((1, 61, 77, 2), 203, "bsf", "1,1", "1,1"), ((1, 109, 77, 5), 2051, "bsf", "1,2", "1,2"),
+    ((1, 237, 77, 7), 2051, "bsf", "1,4", None), ((1, 237, 130, 9), 2051, "bsf", None, "1,4"),
+    ((16, 125, 77, 1), 100, "bsf", "2,1", "2,1"), ((16, 109, 77, 2), 500, "bsf", "2,2", "2,2"),
+    ((16, 109, 77, 2), 1001, "bsf", "2,4", "2,4"), ((16, 109, 13, 2), 1001, "bsf", "2,4", "2,4"),
+    ((1, 29, 77, 1), 31, "bsf", "0,1", "0,1"), ((2, 29, 77, 12), 7, "bsf", "0,4", "0,2"),
+    ((1, 33, 33, 4096), 5, "bsf", "0,4", "0,2")]
+
+
+MASKED_RUNS = [c[:3] + (dtype, c[3 if dtype == "f32" else 4]) for c in MASKED_INSTANCES
+               for dtype in ("f32", "bf16", "f16") if c[3 if dtype == "f32" else 4]]
+
+
+@pytest.mark.parametrize("run", MASKED_RUNS, ids=["%s-%d-%s-%s" % r[:4] for r in MASKED_RUNS])
+@pytest.mark.parametrize("epi", [False, True])
+def test_masked_instances(run, epi):
+    """Each instance at a call the planner gives it, plain and with bias and
+    GELU, the whole output against the oracle."""
+    import torch
+    pattern, batch, layout, dtype, want = run
+    a, b, c, d = pattern
+    M = a * b * d
+    desc = ks.ks_plan_describe(*pattern, batch, layout, dtype)
+    name = "ks_masked_kernel" if want.startswith("0,") else "ks_masked_%s_kernel" % layout
+    t = {"f32": "float", "bf16": "unsignedshort", "f16": "_Float16"}[dtype]
+    assert desc.endswith("kernel=%s<%s,%s,false>" % (name, t, want)), desc
+    if not epi:
+        check(pattern, batch, dtype, layout, cfg=29, kdist="normal")
+        return
+    x, kv, _, _ = case(29, pattern, batch, dtype, "normal", "normal")
+    bias = inputs.round_to(np.random.default_rng(M + batch).standard_normal(M), dtype)
+    yd = nan_tensor((batch * M,), dtype)
+    ks.ks_matmul_bias_act(a, b, c, d, to_device(kv, dtype), to_device(bias, dtype), "gelu",
+                          to_device(inputs.to_layout(x, layout), dtype), yd, batch, layout, dtype)
+    torch.cuda.synchronize()
+    y = inputs.from_layout(from_device(yd, dtype).reshape((batch, M) if layout == "bsf" else (M, batch)), layout)
+    y64 = oracle.bias_act(oracle_y(29, pattern, batch, dtype, "normal", "normal"), inputs.to_f64(bias, dtype), "bsf",
+                          "gelu")
+    err = rel_err(y, y64)
+    assert err <= TOL[dtype], "%s: rel err %.3e" % (desc, err)
+
 # --- bias + GELU epilogue (ks_matmul_bias_act) --------------------------------
 
 EPI_CASES = [("generic", (2, 4, 4, 2), "bsl", 40), ("valu_bsl", (2, 4, 4, 2), "bsl", 64),
