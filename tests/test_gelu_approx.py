@@ -2,12 +2,15 @@
 
 The kernel evaluates GELU(x) = max(x, 0) - |x| Phi(-|x|) with the normal tail
 Phi(-|x|) = u * 2^(-log2(e) x^2 / 2 + R(u)), u = 1 / (2 + |x| / sqrt 2), and R
-a degree-9 polynomial whose coefficients are float literals in the header.
+a degree-9 polynomial whose coefficients are float literals in the header, as
+max(x, 0) - (|x| u) * 2^(...) with |x| u = 0 where u = 0.
 These tests read those literals, check that gelu_fit.py reproduces them, and
 evaluate the same operation sequence in float32 on the CPU (each fused
 multiply-add rounded once; the reciprocal and the power of two correctly
 rounded, where the hardware's are within 1 ulp) against scipy's erfc in float64
-and against the oracle's epilogue.  The GPU parity tests then compare the
+and against the oracle's epilogue.  The statements of the kernel that the
+sequence stands for are compared as text, so that a change there fails here
+until the sequence follows it.  The GPU parity tests then compare the
 kernels themselves with the oracle."""
 import importlib.util
 import os
@@ -38,16 +41,31 @@ def gelu_f32_emulated(x, prefix="kGeluR"):
         return (a.astype(np.float64) * b.astype(np.float64) + np.float64(d) if np.ndim(d) == 0
                 else a.astype(np.float64) * b.astype(np.float64) + d.astype(np.float64)).astype(np.float32)
 
-    xc = np.clip(x, f(-16), f(16))
-    ax = np.abs(xc)
-    u = (1.0 / fma(ax, np.full_like(ax, f(0.70710678118654752)), f(2.0)).astype(np.float64)).astype(np.float32)
-    r = np.full_like(u, c[-1])
-    for ck in c[-2::-1]:
-        r = fma(r, u, ck)
-    t = fma((xc * f(-0.72134752044448170)).astype(np.float32), xc, r)
-    tail = (u * np.exp2(t.astype(np.float64)).astype(np.float32)).astype(np.float32)
-    with np.errstate(invalid="ignore"):
-        return fma(-ax, tail, np.maximum(x, f(0)))
+    ax = np.abs(x)
+    with np.errstate(all="ignore"):
+        u = (1.0 / fma(ax, np.full_like(ax, f(0.70710678118654752)), f(2.0)).astype(np.float64)).astype(np.float32)
+        r = np.full_like(u, c[-1])
+        for ck in c[-2::-1]:
+            r = fma(r, u, ck)
+        e = np.exp2(fma((x * f(-0.72134752044448170)).astype(np.float32), x, r).astype(np.float64)).astype(np.float32)
+        axu = np.where(u == 0, f(0), (ax * u).astype(np.float32))  # v_mul_legacy_f32: 0 times anything is 0
+        return fma(-axu, e, np.fmax(x, f(0)))
+
+
+def test_emulated_statements_are_the_kernels():
+    text = " ".join(open(os.path.join(CSRC, "ks_epilogue.h")).read().split())
+    body = text[text.index("float gelu_f32(float x) {"):]
+    body = body[:body.index("// Single-output form")]
+    statements = ["u = __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(x), 0.70710678118654752f, 2.0f));",
+                  "r = __builtin_fmaf(gelu_reg(kGeluR9), u, kGeluR8);", "r = __builtin_fmaf(gelu_reg(kGeluS5), u, kGeluS4);",
+                  "e = __builtin_amdgcn_exp2f(__builtin_fmaf(x * -0.72134752044448170f, x, r));",
+                  "relu = __builtin_amdgcn_fmed3f(x, 0.0f, gelu_reg(__builtin_inff()));",
+                  "return __builtin_fmaf(-gelu_mul0(x, u, r), e, relu);"]
+    statements += ["r = __builtin_fmaf(r, u, kGeluR%d);" % k for k in range(8)]
+    statements += ["r = __builtin_fmaf(r, u, kGeluS%d);" % k for k in range(4)]
+    assert [s for s in statements if s not in body] == []
+    assert body.count(";") == len(statements) + 1  # and the declaration of r
+    assert 'asm("v_mul_legacy_f32 %0, |%1|, %2" : "=v"(v) : "v"(x), "v"(u), "v"(r));' in text
 
 
 def test_coefficients_match_fit_script():
@@ -105,6 +123,17 @@ def test_gelu_special_values():
     assert y[2] == np.inf and y[3] == 0.0
     np.testing.assert_allclose(y[4:6], 0.5 * x[4:6], rtol=1e-6)
     assert y[8] == np.float32(40.0) and y[9] == 0.0
+    for prefix in ("kGeluR", "kGeluS"):
+        y = gelu_f32_emulated(np.array([np.inf, -np.inf, 3e38, -3e38, np.nan], dtype=np.float32), prefix)
+        assert y[0] == np.inf and y[1] == 0.0 and y[2] == np.float32(3e38) and y[3] == 0.0 and np.isnan(y[4])
+
+
+def test_gelu_far_tails():
+    # no clamp of x: from |x| = 16 on the power of two is 0 and R stays finite
+    x = np.concatenate([np.geomspace(14.0, 3.4e38, 100_001), -np.geomspace(14.0, 3.4e38, 100_001)]).astype(np.float32)
+    for prefix in ("kGeluR", "kGeluS"):
+        y = gelu_f32_emulated(x, prefix)
+        assert np.all(y[x > 0] == x[x > 0]) and np.all(np.abs(y[x < 0]) < 1e-38)
 
 
 def test_gelu_against_oracle_epilogue():
