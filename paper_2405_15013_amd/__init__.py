@@ -125,7 +125,7 @@ def _load_fast(lib):
         from . import _ks_torch
         _ks_torch.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
                         for name in ("ks_matmul", "ks_matmul_bias_act", "ks_chain", "ks_chain_workspace_bytes")},
-                       torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+                       torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, str(torch.__version__))
     except (ImportError, AttributeError):  # not built, or built for another PyTorch
         return
     _fast = _ks_torch

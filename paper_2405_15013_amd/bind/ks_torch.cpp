@@ -20,6 +20,8 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 
+#include <string>
+
 #include "../../include/ks.h"
 
 namespace {
@@ -239,10 +241,20 @@ PyObject* fast_chain(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
 }
 
-// init({name: address of the libks.so function}, _cuda_getDevice, _cuda_getCurrentRawStream)
+// The PyTorch whose class layouts are compiled in.
+const char built_for[] = "built for PyTorch " KS_TORCH_VERSION ";";
+
+// init({name: address of the libks.so function}, _cuda_getDevice, _cuda_getCurrentRawStream,
+// torch.__version__)
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 3 || !PyDict_Check(a[0])) {
-    PyErr_SetString(PyExc_TypeError, "init(addresses, device, stream)");
+  if (n != 4 || !PyDict_Check(a[0]) || !PyUnicode_Check(a[3])) {
+    PyErr_SetString(PyExc_TypeError, "init(addresses, device, stream, version)");
+    return nullptr;
+  }
+  const char* version = PyUnicode_AsUTF8(a[3]);
+  if (!version) return nullptr;
+  if ("built for PyTorch " + std::string(version) + ";" != built_for) {
+    PyErr_Format(PyExc_ImportError, "_ks_torch was %s this is %U", built_for, a[3]);
     return nullptr;
   }
   auto address = [&](const char* name) -> void* {

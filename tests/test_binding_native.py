@@ -24,6 +24,42 @@ def test_leaves_other_arguments_to_the_python_code():
         ks.chain(x, [((2, 4, 4, 2), k)], "bsf")
 
 
+def test_module_of_another_pytorch_is_left_alone(monkeypatch):
+    """The module holds PyTorch's class layouts: another version's is neither
+    loaded nor taken for current."""
+    from paper_2405_15013_amd import build
+    lib = ks.load_library()
+    assert ks._fast is not None and build._bind_is_current()
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "0.0.1")
+        m.setattr(ks, "_fast", None)
+        ks._load_fast(lib)
+        assert ks._fast is None
+        assert not build._bind_is_current()
+
+
+def test_library_is_linked_before_the_module(monkeypatch, tmp_path):
+    """libks.so needs neither PyTorch nor the host compiler: it is there when
+    the module cannot be built, and without PyTorch that is no error."""
+    import importlib.util
+
+    from paper_2405_15013_amd import build
+    src = tmp_path / "one.cpp"
+    src.write_text("int one() { return 1; }\n")
+    monkeypatch.setattr(build, "sources", lambda: [str(src)])
+    monkeypatch.setattr(build, "BUILD", str(tmp_path / "obj"))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libks.so"))
+
+    def fails(incremental=False):
+        raise RuntimeError("no compiler")
+    monkeypatch.setattr(build, "_build_bind", fails)
+    with pytest.raises(RuntimeError, match="no compiler"):
+        build.build(verbose=False)
+    assert (tmp_path / "libks.so").exists()
+    monkeypatch.setattr(importlib.util, "find_spec", lambda name: None)
+    build.build(verbose=False)
+
+
 @pytest.fixture
 def python_form(monkeypatch):
     """Runs a call through the Python form."""
