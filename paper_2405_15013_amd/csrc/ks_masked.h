@@ -1,7 +1,7 @@
 // Masked register-direct MFMA kernel (index arithmetic and decomposition in
 // ks_masked_index.h), batch-size-first: patterns whose b or c is not a multiple
 // of 16, or buffers that are not 16-byte aligned, with rows too long for the
-// LDS tile of ks_ragged.h.
+// LDS tile of ks_ragged.h, or too few of them to be worth it (ragged_bsf_pays).
 #pragma once
 #include "ks_direct.h"
 #include "ks_masked_index.h"
@@ -18,16 +18,14 @@ __device__ __forceinline__ void kernarg_fetch(const Problem& p, const MaskedTile
 
 namespace ks {
 
-// V consecutive elements of type T (V * sizeof(T) bytes, aligned to that).
+// V consecutive elements of type T, as one access where they are 16 bytes
+// (aligned to that).
 template <typename T, int V>
 __device__ __forceinline__ void masked_load(const T* p, T (&v)[V]) {
   constexpr int NB = V * (int)sizeof(T);
   if constexpr (NB == 16) {
     const u32x4 w = *reinterpret_cast<const u32x4*>(p);
     __builtin_memcpy(v, &w, 16);
-  } else if constexpr (NB == 8) {
-    const u32x2 w = *reinterpret_cast<const u32x2*>(p);
-    __builtin_memcpy(v, &w, 8);
   } else {
 #pragma unroll
     for (int e = 0; e < V; ++e) v[e] = p[e];
@@ -40,10 +38,6 @@ __device__ __forceinline__ void masked_store(T* p, const T (&v)[V]) {
     u32x4 w;
     __builtin_memcpy(&w, v, 16);
     __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
-  } else if constexpr (NB == 8) {
-    u32x2 w;
-    __builtin_memcpy(&w, v, 8);
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(p));
   } else {
 #pragma unroll
     for (int e = 0; e < V; ++e) p[e] = v[e];
@@ -56,10 +50,11 @@ __device__ __forceinline__ uint32_t masked_bits(_Float16 v) { return __builtin_b
 
 template <typename T, int LAYOUT, int V, bool EPI>
 __global__ __launch_bounds__(256) void ks_masked_kernel(Problem p, MaskedTile t) {
+  static_assert(LAYOUT == BSF, "batch-size-last calls run ks_ragged.h's kernel");
   constexpr int S = sizeof(T);
   constexpr int LP = S == 4 ? 4 : 8;
   constexpr int CH = 4 * LP;
-  constexpr int VK = LAYOUT == BSL ? 1 : V;  // K blocks per lane (BSF: one per j of the piece)
+  constexpr int VK = V;  // K blocks per lane, one per j of the piece
   const int lane = threadIdx.x & 63;
   // Spare waves of the last workgroup work on the last item and store
   // nothing: no branch before the loads, one round of kernel-argument loads.
@@ -138,18 +133,16 @@ __global__ __launch_bounds__(256) void ks_masked_kernel(Problem p, MaskedTile t)
   }
   if (!live) return;
   // Epilogue (EPI instances only): output feature of (e, r) is row
-  // k = k0 + 4g + r of block (i, j0 [+ e in BSF]); padding rows (k >= b) take
-  // no bias.
+  // k = k0 + 4g + r of block (i, j0 + e); padding rows (k >= b) take no bias.
   if constexpr (EPI) {
-    constexpr int BV = LAYOUT == BSF ? V : 1;
     const bool has_bias = p.bias != nullptr;
-    float bv[4][BV];
+    float bv[4][V];
     if (has_bias) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int k = it.k0 + 4 * g + r;
 #pragma unroll
-        for (int e = 0; e < BV; ++e)
+        for (int e = 0; e < V; ++e)
           bv[r][e] = k < p.b ? bias_value<T>(p, ((int64_t)it.i * p.b + k) * p.d + it.j0 + e) : 0.0f;
       }
     }
@@ -158,7 +151,7 @@ __global__ __launch_bounds__(256) void ks_masked_kernel(Problem p, MaskedTile t)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int e = 0; e < V; ++e) acc[0][e][r] += bv[r][LAYOUT == BSF ? e : 0];
+        for (int e = 0; e < V; ++e) acc[0][e][r] += bv[r][e];
     }
     if (epilogue_gelu(p)) {
 #pragma unroll
@@ -181,21 +174,27 @@ __global__ __launch_bounds__(256) void ks_masked_kernel(Problem p, MaskedTile t)
   }
 }
 
-// Instances of one storage type: V in {1, 2, 4} (and 8 for 16-bit BSL).
+// Instances of one storage type: the widths masked_vec() picks, single elements
+// and 16 bytes in fp32, one and two elements in 16 bits.
 // EPI: the bias / activation epilogue compiled in (calls that need it).
 template <typename T>
 hipError_t launch_masked_type(const Problem& p, const MaskedTile& t, int V, unsigned grid, hipStream_t s) {
   const dim3 g(grid), b(256);
   const bool epi = has_epilogue(p);
-#define KS_MASKED(L, VV)                                                              \
-  if (p.layout == L && V == VV) {                                                     \
+#define KS_MASKED(VV)                                                                 \
+  if (p.layout == BSF && V == VV) {                                                   \
     if (epi)                                                                          \
-      hipLaunchKernelGGL((ks_masked_kernel<T, L, VV, true>), g, b, 0, s, p, t);      \
+      hipLaunchKernelGGL((ks_masked_kernel<T, BSF, VV, true>), g, b, 0, s, p, t);    \
     else                                                                              \
-      hipLaunchKernelGGL((ks_masked_kernel<T, L, VV, false>), g, b, 0, s, p, t);     \
+      hipLaunchKernelGGL((ks_masked_kernel<T, BSF, VV, false>), g, b, 0, s, p, t);   \
     return hipGetLastError();                                                         \
   }
-  KS_MASKED(BSF, 1) KS_MASKED(BSF, 2) KS_MASKED(BSF, 4)
+  KS_MASKED(1)
+  if constexpr (sizeof(T) == 4) {
+    KS_MASKED(4)
+  } else {
+    KS_MASKED(2)
+  }
 #undef KS_MASKED
   return hipErrorInvalidValue;
 }
