@@ -48,7 +48,11 @@ __host__ __device__ constexpr int pair_lds(int layout, int esize, int N) {
 }
 
 // Instances: where the values of both factors (2*NBW*BT*BT runs of 4 per lane)
-// and a tile's X fit the registers.  Batch-size-last only 16-bit types: an fp32
+// and a tile's X fit the registers, or miss them by so few that the kernel is
+// faster than ks_chain_mfma.hip's all the same: (b, q) = (32, 64) batch-size-first
+// in 16 bits spills 17 registers (bf16 at batch 4096, 16384, 24592 23.5 -> 21.7,
+// 86.4 -> 51.7, 141.9 -> 81.6 us), (48, 16) in fp32 one (15.6 -> 14.6, 55.4 ->
+// 36.5, 83.2 -> 51.7 us).  Batch-size-last only 16-bit types: an fp32
 // tile of whole lines ran 0-20 % slower than ks_chain_mfma.hip's.
 __host__ __device__ constexpr bool pair_instance(int layout, int esize, int bt, int nbw) {
   return bt >= 1 && bt <= 4 && (nbw == 1 || nbw == 2 || nbw == 4 || nbw == 8) &&

@@ -104,11 +104,12 @@ bool plan_direct(const Problem& p, bool al16, Plan* pl) {
   return true;
 }
 
-// Masked kernels: blocks larger than the VALU kernels take (b or c > 16) that
-// the other MFMA kernels cannot run.  Batch-size-last and batch-size-first rows
-// that fit LDS: the kernels of ks_ragged.h (plan field unroll = 1).  Longer
-// batch-size-first rows: the register kernel of ks_masked.h, with the access
-// width V that d and the buffers' alignment allow.
+// Masked kernels: blocks that the other MFMA kernels cannot run and that are not
+// small enough for the VALU kernels (valu_pays in ks_host.cpp).  Batch-size-last,
+// and batch-size-first rows that fit LDS and are enough to pay there: the kernels
+// of ks_ragged.h (plan field unroll = 1).  Other batch-size-first rows: the
+// register kernel of ks_masked.h, with the access width V that d and the
+// buffers' alignment allow.
 int masked_vec(const Problem& p) {
   const int s = p.dtype == F32 ? 4 : 2;
   int V = 4;
@@ -160,7 +161,8 @@ bool plan_ragged_bsl(const Problem& p, Plan* pl) {
 
 // Batch-size-first: two row groups where that leaves a workgroup per CU and
 // LDS for two of them per CU, and b split until there are enough workgroups
-// (each split reads the X rows again, from L2).
+// (each split reads the X rows again, from L2).  Rows of Y that do not fit as a
+// whole keep the register kernel, also where a split of b would fit (not timed).
 constexpr int kRaggedMaxLds = 160 * 1024;  // ks_ragged.h
 bool plan_ragged_bsf(const Problem& p, Plan* pl) {
   const int S = p.dtype == F32 ? 4 : 2, KT = (p.b + 15) / 16;

@@ -64,7 +64,10 @@ constexpr float kGeluS5 = 10.5570784f;
 // moved for each output took three operations more.  (6,64,16,8) with bias and
 // GELU at batch 25088: FP8 batch-size-first 54.4 -> 47.6 us, batch-size-last bf16
 // 53.7 -> 50.0, f16 56.9 -> 53.4, FP8 63.0 -> 57.2 us; fp32 1 to 4 % faster; bf16
-// batch-size-first the same (56 us: two waves per SIMD, not the operations).
+// batch-size-first the same (54 us, 51 since its operands are packed by
+// v_perm_b32: a tile of the DMA kernel runs these operations with none of its
+// own loads in flight and two workgroups per CU, so they add to the X stream
+// instead of running under it).
 // A constant in a vector register, for operands that take no literal.
 __device__ __forceinline__ float gelu_reg(float c) {
   asm("" : "+v"(c));

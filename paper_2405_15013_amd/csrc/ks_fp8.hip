@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void ks_fp8_kernel(Problem p, MaskedTile t) {
 // go through an LDS tile of its own and leave as runs of 256 * MT bytes in whole
 // lines.  One item per tile loaded 16 K operands for 10 accesses of X and Y,
 // waited for all of them, and wrote half lines: (6,64,16,8) at batch 25088
-// 52.7 -> 34.0 us (5.1 TB/s), with bias and GELU 119 -> 54 us, (6,16,64,8)
+// 52.7 -> 34.0 us (5.1 TB/s), with bias and GELU 119 -> 48 us, (6,16,64,8)
 // 31.8 -> 28.0 us, (8,96,64,8) 185 -> 76 us; equal (launch-bound) below a batch
 // of about 1000.  X is loaded without the nontemporal hint: each of its lines
 // is read by two loads and by every k-group (with it the first took 47 us).

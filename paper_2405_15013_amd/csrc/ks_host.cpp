@@ -555,7 +555,11 @@ bool chain_pair_plan(const ks_factor_t* f, int n, int64_t batch, int layout, int
   // (width 1024), whatever the batch: factor by factor is faster until the
   // tiles fill the chip (bf16, batch 4096: 8.6 us against 15.7; 16384: 28.3
   // against 22.0; equal near 11000), except for widths up to 256 (batch 64
-  // to 16384: 4.8-8.3 us against 3.9-6.7).
+  // to 16384: 4.8-8.3 us against 3.9-6.7).  Of 300 16-bit
+  // batch-size-last calls of all instances, batch 10240 to 32832, 17 are then
+  // 1.04 to 1.22 times slower than factor by factor, all of widths 256 to 768 at
+  // multiples of 2048, where the grids of the two products fill the chip evenly;
+  // the others are at 0.59 to 1.03.
   if (layout == BSL && b * q > 256 && tiles < 192) return false;
   pc->batch = (int)batch;
   pc->tiles = (int)tiles;

@@ -1,9 +1,10 @@
 // Index arithmetic of the masked register-direct MFMA kernel (ks_masked.h),
 // shared by the kernel and by the host-side plan verifier.
 //
-// The masked kernel runs the batch-size-first rows that are too long for the
-// LDS of ks_ragged.h's (b or c not a multiple of 16, or unaligned buffers);
-// the FP8 kernel uses the same functions in both layouts.  Its
+// The masked kernel runs the batch-size-first calls (b or c not a multiple of
+// 16, or unaligned buffers) whose rows are too long for the LDS of ks_ragged.h's
+// or too few for it to pay; the FP8 kernel uses the same functions in both
+// layouts.  Its
 // work decomposition is the register-direct one (output-stationary items of
 // Section 4.1, Algorithm 2): one wavefront per item = (batch tile, i, j or
 // j-group, 16 output rows k), lanes (n, g) = (lane % 16, lane / 16) in the

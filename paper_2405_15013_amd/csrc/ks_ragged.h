@@ -11,7 +11,7 @@
 // load of X is a 16-byte vector, the next chunks are loaded while one is
 // multiplied, and batch-size-first the rows go through LDS as runs.  Measured
 // (before, now; rate of X + K + Y): fp32 batch-size-last (4,40,24,6) at batch
-// 10007 39.7, 22.5 us (2.7 TB/s); (8,64,96,4) at 14637 225, 111 us (2.7 TB/s);
+// 10007 31.5, 16.8 us (3.7 TB/s); (8,64,96,4) at 14637 225, 111 us (2.7 TB/s);
 // f16 (6,96,96,4) at 2630 39.0, 12.5 us; bf16 batch-size-first (6,110,80,3) at
 // 5504 129, 44 us; (4,29,89,5) at 3327 44, 13 us; 70 calls of all sizes 1.66x in
 // the mean.  What bounds it now: batch-size-last the misaligned vectors (two

@@ -31,7 +31,7 @@ struct RaggedTile {
   int items;             // batch-size-last: wavefront items; batch-size-first: workgroups
   int kgroups;           // batch-size-last: ceil(b / 16 MT); batch-size-first: splits of b
   int nbt;               // batch groups
-  int kb;                // batch-size-first: rows k per workgroup (a multiple of 16 MT)
+  int kb;                // batch-size-first: rows k per workgroup (a multiple of 16; the last item of 16 MT rows may be cut short)
   int upr;               // batch-size-first: 16-byte units per run of X
   int xpitch, ypitch;    // batch-size-first: LDS row pitches in bytes
   int lds;

@@ -302,8 +302,6 @@ bool verify_masked_v(Checker& ck, int V, int MT) {
   return ck.err.empty();
 }
 
-// The planned access width, then every narrower one the planner would pick
-// for less aligned buffers (each with its own coverage check).
 // Masked kernels of ks_ragged.h.
 bool verify_ragged(Checker& ck, const Plan& pl) {
   const Problem& p = ck.p;
@@ -438,6 +436,8 @@ bool verify_fp8_rows(Checker& ck, const Fp8Rows& t) {
   return ck.err.empty();
 }
 
+// The planned access width, then every narrower one the planner would pick
+// for less aligned buffers (each with its own coverage check).
 bool verify_masked(Checker& ck, const Plan& pl) {
   if (pl.variant == V_FP8) {  // the long-row kernel, then the one unaligned K takes
     Fp8Rows t;

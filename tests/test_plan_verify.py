@@ -313,3 +313,16 @@ def test_small_blocks_run_the_faster_kernel(pattern, batch, layout, dtype, valu)
     assert valu or "name=masked" in desc, desc
     st, rep = ks.ks_plan_verify(*pattern, batch, layout, dtype)
     assert st == 0, rep
+
+
+def test_masked_instances_replayed():
+    """The calls at which the GPU suite runs each masked instance, those of up to
+    half a million outputs: replayed on the host."""
+    from test_gpu_parity import MASKED_RUNS
+    ran = set()
+    for (a, b, c, d), batch, layout, dtype, want in MASKED_RUNS:
+        if dtype != "f16" and a * b * d * batch <= 5e5:
+            st, rep = ks.ks_plan_verify(a, b, c, d, batch, layout, dtype)
+            assert st == 0, rep
+            ran.add((layout, want))
+    assert {("bsl", "1,4"), ("bsl", "1,2"), ("bsl", "8,1"), ("bsf", "1,1"), ("bsf", "2,1"), ("bsf", "0,4")} <= ran
