@@ -16,6 +16,7 @@ distance; they are checked only for being read by that instruction first.
 """
 import concurrent.futures
 import os
+import re
 import subprocess
 import tempfile
 
@@ -120,3 +121,18 @@ def test_kernel_arguments_arrive_in_one_round(kernel_asm):
     assert checked > 250 and dma > 250
     assert not bad, bad[:10]
     assert dma_one >= 0.9 * dma, (dma_one, dma)
+
+
+def test_single_pieces_are_stored_without_the_streaming_hint(kernel_asm):
+    """Register-direct batch-size-first instances whose lane has one piece per row
+    tile (d = 1, in 16 bits also d = 2): plain stores."""
+    seen = 0
+    for f, fns in kernel_asm.items():
+        for fn, lines in fns.items():
+            m = re.search(r"ks_direct(?:_c)?_kernelI(f|t|DF16_)Li0ELi(\d)ELb0E", fn)
+            if not m or m.group(2) not in ("1" if m.group(1) == "f" else "12"):
+                continue
+            stores = [ln for ln in lines if ln.startswith("global_store_dwordx")]
+            assert stores and all(ln.split()[-1] != "nt" for ln in stores), fn
+            seen += 1
+    assert seen > 200
