@@ -235,17 +235,23 @@ bool plan_masked_reg(const Problem& p, Plan* pl) {
 // workgroups that chain is the call's time ((2,3,34,37) fp32 at batch 104 4.5 us
 // in registers, 13.5 us through LDS; (3,29,2,228) bf16 at batch 1 3.8, 41.9 us),
 // with many the shared X rows and whole-line stores win (down to 0.17 of the
-// register kernel's time).  Timed both ways on 878 calls with b or c above 16
-// (batch 1 to 30000, fp32 and bf16): below 16 batch rows the LDS form is slower
-// unless a wavefront has one product of a long sum; above, it pays from eight
-// workgroups per product of the chain, with at least 6 KB of rows to share.  Of
-// those calls this rule leaves 36 more than 5 % behind the register kernel alone
-// (without it 219) and the mean at 0.71 of its time.
+// register kernel's time).  Timed both ways on 2500 calls with b or c above 16
+// (batch 1 to 4000, fp32, bf16, f16, with and without the epilogue): below 16
+// batch rows the LDS form is slower unless a wavefront has one product of a long
+// sum.  Above, with at least 6 KB of rows to share, it pays where the register
+// kernel has 2500 wavefronts and more, so that its gathers and not their latency
+// are what it waits for, from eight workgroups per product of the chain; with
+// fewer wavefronts, from 32 per product and sums of 36.  This leaves 17 of those
+// calls more than 5 % behind the register kernel, one more than 1.2 times
+// (eight workgroups per product alone: 88, 33), and the mean at 0.72 of its time.
 bool ragged_bsf_pays(const Problem& p, const Plan& pl) {
   const int kgroups = (pl.kgw + pl.waves_m - 1) / pl.waves_m;
   const int64_t chain = ((int64_t)kgroups * p.d + 3) / 4;  // products per wavefront
   if (p.batch < 16) return chain == 1 && p.c >= 64;
-  return pl.grid >= 8 * chain && pl.lds_bytes >= 6000;
+  if (pl.lds_bytes < 6000) return false;
+  if (pl.grid >= 32 * chain && p.c >= 36) return true;
+  const MaskedTile t = masked_tile(p, masked_vec(p));
+  return pl.grid >= 8 * chain && (int64_t)t.nbt * p.a * t.jgroups * t.kgroups >= 2500;
 }
 
 // The masked kernel when it is asked for: ks_ragged.h's wherever it can run.

@@ -287,6 +287,8 @@ def test_plans_of_many_blocks_can_be_launched(pattern, batch, layout, dtype):
 @pytest.mark.parametrize("pattern,batch,dtype,lds", [
     ((3, 29, 2, 228), 1, "bf16", False), ((2, 3, 34, 37), 104, "f32", False), ((1, 33, 33, 16), 8, "f32", False),
     ((21, 33, 4, 9), 6, "bf16", False), ((1, 115, 28, 37), 26, "f32", False), ((2, 40, 130, 1), 4, "f32", True),
+    ((6, 30, 17, 21), 49, "bf16", False), ((7, 23, 31, 14), 41, "f32", False), ((2, 160, 3, 30), 51, "f16", False),
+    ((1, 129, 12, 7), 64, "f16", False), ((16, 125, 77, 1), 100, "bf16", True),
     ((1, 33, 33, 16), 4096, "f32", True), ((6, 110, 80, 3), 5504, "bf16", True), ((4, 29, 89, 5), 3327, "bf16", True)])
 def test_masked_rows_through_lds_where_there_are_enough(pattern, batch, dtype, lds):
     """Batch-size-first masked calls: rows through LDS only with the workgroups
