@@ -258,9 +258,9 @@ bool dma_k_through_lds(const Problem& p) {
     default: return false;
   }
 }
-DmaPrefs dma_prefs(const Problem& p) {
+DmaPrefs dma_prefs(const Problem& p, bool klds) {
   const bool f32 = p.dtype == F32;
-  if (dma_k_through_lds(p)) return {f32 && p.d >= 16 && p.b >= 64 ? 128 * 1024 : 80 * 1024, f32 ? 4 : 2, true};
+  if (klds) return {f32 && p.d >= 16 && p.b >= 64 ? 128 * 1024 : 80 * 1024, f32 ? 4 : 2, true};
   // fp32 with d = 16, b >= 64 and c >= 48: the 64 KB preference would leave
   // 16-row tiles (four j-groups take the four wavefronts) whose stages hold too
   // few MFMAs to cover the next stage's K loads; 32-row tiles in up to 128 KB
@@ -345,16 +345,13 @@ bool plan_dma_bsl(const Problem& p, bool al16, Plan* pl) {
   return true;
 }
 
-bool plan_dma(const Problem& p, bool al16, Plan* pl) {
-  if (p.layout == BSL) return plan_dma_bsl(p, al16, pl);
-  if (!al16 || p.layout != BSF || p.b % 16 || p.c % 16) return false;
-  if (p.d != 1 && p.d != 2 && p.d != 4 && p.d != 8 && p.d != 16) return false;
+namespace {
+// The preferred tile for a batch-size-first call.
+bool dma_choose(const Problem& p, const DmaPrefs& prefs, DmaChoice* best) {
   const int S = p.dtype == F32 ? 4 : 2;
   const int V = p.d < 4 ? p.d : 4, JG = p.d / V, W = 4;
   const int KT = p.b / 16;
-  const DmaPrefs prefs = dma_prefs(p);
   bool found = false;
-  DmaChoice best{};
   // 16-bit types: 16x16x32 MFMAs (LP = 8, stages of 32 values of l) when
   // c % 32 == 0, or 16x16x16 (LP = 4, stages of 16: half the stage size).
   for (int LP = (S == 2 && p.c % 32 == 0) ? 8 : 4; LP >= 4; LP /= 2) {
@@ -381,14 +378,39 @@ bool plan_dma(const Problem& p, bool al16, Plan* pl) {
           const int64_t tiles = (int64_t)((p.batch + span - 1) / span) * p.a * kgt;
           if (tiles > 0x7fffffff) continue;
           const DmaChoice c{LP, mt, nt, kgw, rs, kgt, klds, tiles, lds};
-          if (!found || dma_better(c, best, prefs)) {
+          if (!found || dma_better(c, *best, prefs)) {
             found = true;
-            best = c;
+            *best = c;
           }
         }
       }
     }
   }
+  return found;
+}
+
+// fp32 with d = 8 and K in LDS: tiles of two M-tiles and two row groups, twice as
+// long as those with K in registers.  A CU works through its tiles at a pace that
+// two of them at once do not raise, so where the tiles leave CUs a whole tile
+// apart ((6,128,96,8) at batch 704: 264 tiles, 18.1 -> 21.8 us) the shorter ones
+// are faster: of 1500 calls those with more than 1.25 times the even share of
+// tiles on the fullest CU were at 1.14 of the time with K in registers (1.28 the
+// most, 24 of 27 behind), the others at 0.95; other d, M-tiles and types 0.8 to
+// 0.93 at any share.
+bool dma_uneven(const Problem& p, const DmaChoice& c) {
+  if (p.dtype != F32 || p.d != 8 || !c.klds || c.mt != 2 || c.tiles <= 256) return false;
+  return (c.tiles + 255) / 256 * 256 * 4 > 5 * c.tiles;
+}
+}  // namespace
+
+bool plan_dma(const Problem& p, bool al16, Plan* pl) {
+  if (p.layout == BSL) return plan_dma_bsl(p, al16, pl);
+  if (!al16 || p.layout != BSF || p.b % 16 || p.c % 16) return false;
+  if (p.d != 1 && p.d != 2 && p.d != 4 && p.d != 8 && p.d != 16) return false;
+  const int V = p.d < 4 ? p.d : 4, JG = p.d / V, W = 4;
+  DmaChoice best{};
+  bool found = dma_choose(p, dma_prefs(p, dma_k_through_lds(p)), &best);
+  if (found && dma_uneven(p, best)) found = dma_choose(p, dma_prefs(p, false), &best);
   if (!found) return false;
   pl->variant = V_DMA;
   pl->vec = V;

@@ -328,3 +328,15 @@ def test_masked_instances_replayed():
             assert st == 0, rep
             ran.add((layout, want))
     assert {("bsl", "1,4"), ("bsl", "1,2"), ("bsl", "8,1"), ("bsf", "1,1"), ("bsf", "2,1"), ("bsf", "0,4")} <= ran
+
+
+@pytest.mark.parametrize("pattern,batch,klds", [
+    ((6, 128, 96, 8), 600, True), ((6, 128, 96, 8), 704, False), ((6, 128, 96, 8), 1500, False),
+    ((6, 128, 96, 8), 4096, True), ((1, 256, 128, 8), 2571, False), ((1, 256, 128, 16), 2571, True)])
+def test_k_through_lds_not_with_uneven_long_tiles(pattern, batch, klds):
+    """fp32, d = 8: the long tiles of the form with K in LDS only where the CUs get
+    about the same number of them."""
+    desc = ks.ks_plan_describe(*pattern, batch, "bsf", "f32")
+    assert ("kernel=ks_dma_klds_kernel<" in desc) == klds, desc
+    st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", "f32")
+    assert st == 0, rep
