@@ -421,9 +421,10 @@ def test_ragged_edges(pattern, layout, dtype, batch):
 MASKED_INSTANCES = [
     ((16, 61, 77, 32), 7, "bsl", "1,2", "1,2"), ((16, 109, 77, 32), 7, "bsl", "1,4", "1,4"),
     ((16, 61, 77, 32), 31, "bsl", "2,2", "2,2"), ((16, 109, 77, 32), 31, "bsl", "2,4", "2,4"),
-    ((1, 29, 77, 3), 31, "bsl", "2,1", "2,1"), ((16, 61, 77, 32), 33, "bsl", "4,2", "4,2"),
-    ((16, 109, 77, 32), 33, "bsl", "4,4", "4,4"), ((1, 29, 77, 3), 33, "bsl", "4,1", "4,1"),
-    ((6, 77, 37, 5), 2051, "bsl", "4,2", "8,2"), ((1, 29, 77, 3), 130, "bsl", "4,1", "8,1"),
+    ((16, 29, 77, 16), 31, "bsl", "2,1", "2,1"), ((16, 61, 77, 32), 33, "bsl", "4,2", "4,2"),
+    ((16, 109, 77, 32), 33, "bsl", "4,4", "4,4"), ((16, 29, 77, 16), 33, "bsl", "4,1", "4,1"),
+    ((6, 77, 37, 5), 2051, "bsl", "4,2", "8,2"), ((16, 29, 77, 16), 65, "bsl", "4,1", "8,1"),
+    ((1, 29, 77, 3), 130, "bsl", "1,1", "1,1"),
     ((1, 61, 77, 2), 203, "bsf", "1,1", "1,1"), ((1, 109, 77, 5), 2051, "bsf", "1,2", "1,2"),
     ((1, 237, 77, 7), 2051, "bsf", "1,4", None), ((1, 237, 130, 9), 2051, "bsf", None, "1,4"),
     ((16, 125, 77, 1), 100, "bsf", "2,1", "2,1"), ((16, 109, 77, 2), 500, "bsf", "2,2", "2,2"),

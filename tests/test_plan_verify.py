@@ -340,3 +340,15 @@ def test_k_through_lds_not_with_uneven_long_tiles(pattern, batch, klds):
     assert ("kernel=ks_dma_klds_kernel<" in desc) == klds, desc
     st, rep = ks.ks_plan_verify(*pattern, batch, "bsf", "f32")
     assert st == 0, rep
+
+
+@pytest.mark.parametrize("pattern,batch,dtype,vec", [
+    ((1, 96, 16, 8), 65, "f16", 1), ((4, 32, 16, 1), 293, "f16", 1), ((6, 48, 16, 8), 515, "bf16", 8),
+    ((4, 40, 24, 6), 10007, "f32", 4), ((2, 40, 24, 6), 515, "f32", 2), ((2, 40, 24, 6), 515, "bf16", 2)])
+def test_masked_vectors_leave_wavefronts(pattern, batch, dtype, vec):
+    """Batch-size-last masked calls: vectors of the batch no wider than leaves 512
+    wavefronts."""
+    f = dict(x.split("=", 1) for x in ks.ks_plan_describe(*pattern, batch, "bsl", dtype).split())
+    assert f["name"] == "masked" and int(f["vec"]) == vec, f
+    st, rep = ks.ks_plan_verify(*pattern, batch, "bsl", dtype)
+    assert st == 0, rep
