@@ -145,7 +145,7 @@ bool plan_variant(int v, const Problem& p, bool al16, Plan* pl) {
 //    1.02 (above 2 MB; 0.4-0.9 in small ones, where both are near a launch);
 //    twice that b * c 0.55, 0.5, 0.41, 0.55.  Rows left to the register kernel
 //    (ks_masked.h), which gathers them, with d >= 100: half as much again.
-//    Of 3665 calls this leaves 42 more than 5 % behind the VALU kernel (with
+//    Of 3665 calls this leaves 36 more than 5 % behind the VALU kernel (with
 //    b, c > 4 alone as the line 441), the mean at 0.40 of its time.
 //  * batch-size-last: up to 4 x 4; and whole vectors of the batch with b * c
 //    below 32 from 4 MB of X + Y, where the VALU kernel is at the copy rate

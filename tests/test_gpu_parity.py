@@ -280,7 +280,7 @@ def test_dma_full_batch(pattern, dtype):
 # K operands through LDS: j-groups of one wavefront and of four (d = 4, 16),
 # three stages and more, row groups and M-tiles of one and two, c = 160 with
 # five and ten stages.
-DMA_K_LDS_SHAPES = [(2, 128, 96, 8), (1, 96, 128, 4), (2, 48, 128, 16), (1, 32, 128, 16), (1, 16, 128, 8),
+DMA_K_LDS_SHAPES = [(4, 128, 96, 8), (1, 96, 128, 4), (2, 48, 128, 16), (1, 32, 128, 16), (1, 16, 128, 8),
                     (1, 64, 160, 16), (1, 128, 128, 16)]
 
 
