@@ -729,7 +729,8 @@ class Runner:
         t_fused = max(fused / HBM_BW, flops / PEAK[dtype])
         desc = ks.ks_chain_describe(factors, batch, layout, dtype)
         r = {"chain": [list(p) for p in patterns], "batch": batch, "dtype": dtype, "layout": layout,
-             "path": desc.split()[0], "us": t * 1e6, "gbps_unfused": unfused / t / 1e9, "frac_unfused": t_roof / t,
+             "path": "pair" if " pair=1" in desc else desc.split()[0], "us": t * 1e6,
+             "gbps_unfused": unfused / t / 1e9, "frac_unfused": t_roof / t,
              "fused_lower_bound_us": t_fused * 1e6, "frac_fused_bound": t_fused / t,
              "gbps_fused_bytes": fused / t / 1e9}
         if self.per_launch:
