@@ -323,20 +323,14 @@ __device__ __forceinline__ void dma_body(Problem p, StagedTile t) {
           for (int r4 = 0; r4 < 4; ++r4) acc[u][mt][e][r4] += bv[mt][e][r4];
   }
   if (epilogue_gelu(p)) {
-    if constexpr (S == 2) {
-      f32x4* av = &acc[0][0][0];
-      gelu_in_turn<T, 4 * NT * MT * V>([&](int i) { return av[i >> 2][i & 3]; },
-                                       [&](int i, float y) { av[i >> 2][i & 3] = y; });
-    } else {
 #pragma unroll
-      for (int u = 0; u < NT; ++u)
+    for (int u = 0; u < NT; ++u)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-          for (int e = 0; e < V; ++e)
+        for (int e = 0; e < V; ++e)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) acc[u][mt][e][r4] = gelu_f32<T>(acc[u][mt][e][r4]);
-    }
+          for (int r4 = 0; r4 < 4; ++r4) acc[u][mt][e][r4] = gelu_f32<T>(acc[u][mt][e][r4]);
   }
   __syncthreads();  // every wavefront is done with the stage buffers
   char* ycell0 = smem + dma_y_lds_lane(p, t, si, MT, S, n, g);

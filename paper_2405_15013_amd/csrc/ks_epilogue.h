@@ -67,7 +67,13 @@ constexpr float kGeluS5 = 10.5570784f;
 // batch-size-first the same (54 us, 51 since its operands are packed by
 // v_perm_b32: a tile of the DMA kernel runs these operations with none of its
 // own loads in flight and two workgroups per CU, so they add to the X stream
-// instead of running under it).
+// instead of running under it).  Of 500 batch-size-first DMA calls with bias and
+// GELU, batch 500 to 25088, the mean is 0.97 of the longer form's time; fifteen,
+// most with d = 16, are 1.03 to 1.14 times slower ((6,48,32,16) fp32 at batch 13020
+// 128 -> 145 us, (8,64,32,16) f16 at 14208 94 -> 99), although they issue fewer
+// operations.  Putting the next reciprocal and the last power of two under each
+// polynomial by hand gave 137 and 99 us there, 55 -> 52 us in the bf16 call above
+// and 97 -> 102 in the fp32 one: not kept.
 // A constant in a vector register, for operands that take no literal.
 __device__ __forceinline__ float gelu_reg(float c) {
   asm("" : "+v"(c));
@@ -84,82 +90,30 @@ __device__ __forceinline__ float gelu_mul0(float x, float u, float r) {
   return v;
 }
 
-// The steps: u of x, R(u) in two halves, the power of two, the sum.
-__device__ __forceinline__ float gelu_u(float x) {
-  return __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(x), 0.70710678118654752f, 2.0f));
-}
-template <typename OUT>
-__device__ __forceinline__ float gelu_r_head(float u) {
+template <typename OUT = float>
+__device__ __forceinline__ float gelu_f32(float x) {
+  const float u = __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(x), 0.70710678118654752f, 2.0f));
   float r;
   if constexpr (sizeof(OUT) == 4) {
     r = __builtin_fmaf(gelu_reg(kGeluR9), u, kGeluR8);
     r = __builtin_fmaf(r, u, kGeluR7);
     r = __builtin_fmaf(r, u, kGeluR6);
     r = __builtin_fmaf(r, u, kGeluR5);
-  } else {
-    r = __builtin_fmaf(gelu_reg(kGeluS5), u, kGeluS4);
-    r = __builtin_fmaf(r, u, kGeluS3);
-  }
-  return r;
-}
-template <typename OUT>
-__device__ __forceinline__ float gelu_r_tail(float r, float u) {
-  if constexpr (sizeof(OUT) == 4) {
     r = __builtin_fmaf(r, u, kGeluR4);
     r = __builtin_fmaf(r, u, kGeluR3);
     r = __builtin_fmaf(r, u, kGeluR2);
     r = __builtin_fmaf(r, u, kGeluR1);
     r = __builtin_fmaf(r, u, kGeluR0);
   } else {
+    r = __builtin_fmaf(gelu_reg(kGeluS5), u, kGeluS4);
+    r = __builtin_fmaf(r, u, kGeluS3);
     r = __builtin_fmaf(r, u, kGeluS2);
     r = __builtin_fmaf(r, u, kGeluS1);
     r = __builtin_fmaf(r, u, kGeluS0);
   }
-  return r;
-}
-__device__ __forceinline__ float gelu_exp(float x, float r) {
-  return __builtin_amdgcn_exp2f(__builtin_fmaf(x * -0.72134752044448170f, x, r));  // 2^(R(u) - log2(e)/2 x^2)
-}
-__device__ __forceinline__ float gelu_sum(float x, float xu, float e) {
+  const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x * -0.72134752044448170f, x, r));  // 2^(R(u) - log2(e)/2 x^2)
   const float relu = __builtin_amdgcn_fmed3f(x, 0.0f, gelu_reg(__builtin_inff()));
-  return __builtin_fmaf(-xu, e, relu);
-}
-
-template <typename OUT = float>
-__device__ __forceinline__ float gelu_f32(float x) {
-  const float u = gelu_u(x);
-  const float r = gelu_r_tail<OUT>(gelu_r_head<OUT>(u), u);
-  return gelu_sum(x, gelu_mul0(x, u, r), gelu_exp(x, r));
-}
-
-// N values in turn (get(i), set(i, y)): the reciprocal of the next one and the
-// power of two of the one before under the operations of each.  The order that
-// the compiler chooses moves with the code around it, by up to 10 % of a call
-// either way, and can put the transcendentals next to each other with their uses
-// right behind.  Used by the batch-size-first DMA kernels in 16 bits: when their
-// common body became a function, 56 of 553 calls with bias and GELU (batch 500 to
-// 25088) were more than 3 % slower in the compiler's order, 14 are in turn
-// ((6,64,16,8) bf16 at batch 25088 51.1 -> 53.7, in turn 50.8 us), and all are at
-// 0.95 of the time of the longer GELU form in the mean, 14 of them at 1.03 to 1.08.
-// In fp32 the compiler's order is the better one ((6,64,16,8) 97 us, in turn 102).
-template <typename OUT, int N, typename Get, typename Set>
-__device__ __forceinline__ void gelu_in_turn(Get get, Set set) {
-  float u = gelu_u(get(0)), xu = 0.0f, e = 0.0f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const float x = get(i);
-    float r = gelu_r_head<OUT>(u);
-    const float un = i + 1 < N ? gelu_u(get(i + 1 < N ? i + 1 : i)) : 0.0f;
-    __builtin_amdgcn_sched_barrier(0);
-    r = gelu_r_tail<OUT>(r, u);
-    const float en = gelu_exp(x, r), xun = gelu_mul0(x, u, r);
-    if (i > 0) set(i - 1, gelu_sum(get(i > 0 ? i - 1 : 0), xu, e));
-    __builtin_amdgcn_sched_barrier(0);
-    u = un;
-    e = en;
-    xu = xun;
-  }
-  set(N - 1, gelu_sum(get(N - 1), xu, e));
+  return __builtin_fmaf(-gelu_mul0(x, u, r), e, relu);
 }
 
 // Single-output form (bias index m), for kernels with one output per thread.

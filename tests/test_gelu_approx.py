@@ -54,25 +54,18 @@ def gelu_f32_emulated(x, prefix="kGeluR"):
 
 def test_emulated_statements_are_the_kernels():
     text = " ".join(open(os.path.join(CSRC, "ks_epilogue.h")).read().split())
-
-    def body(name):
-        i = text.index(" float %s(" % name)
-        return text[text.index("{", i):text.index(" } ", text.index("return", i))]
-    poly = body("gelu_r_head") + body("gelu_r_tail")
-    for first, name, degree in (("9", "R", 9), ("5", "S", 5)):
-        steps = ["r = __builtin_fmaf(gelu_reg(kGelu%s%s), u, kGelu%s%d);" % (name, first, name, degree - 1)]
-        steps += ["r = __builtin_fmaf(r, u, kGelu%s%d);" % (name, k) for k in range(degree - 2, -1, -1)]
-        at = [poly.index(s) for s in steps]
-        assert at == sorted(at)
-    assert poly.count("r = ") == 14  # 9 and 5 steps
-    for name, statement in (
-            ("gelu_u", "return __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(x), 0.70710678118654752f, 2.0f));"),
-            ("gelu_exp", "return __builtin_amdgcn_exp2f(__builtin_fmaf(x * -0.72134752044448170f, x, r));"),
-            ("gelu_sum", "const float relu = __builtin_amdgcn_fmed3f(x, 0.0f, gelu_reg(__builtin_inff())); "
-                         "return __builtin_fmaf(-xu, e, relu);")):
-        assert statement in body(name), body(name)
+    body = text[text.index("float gelu_f32(float x) {"):]
+    body = body[:body.index("// Single-output form")]
+    statements = ["u = __builtin_amdgcn_rcpf(__builtin_fmaf(__builtin_fabsf(x), 0.70710678118654752f, 2.0f));",
+                  "r = __builtin_fmaf(gelu_reg(kGeluR9), u, kGeluR8);", "r = __builtin_fmaf(gelu_reg(kGeluS5), u, kGeluS4);",
+                  "e = __builtin_amdgcn_exp2f(__builtin_fmaf(x * -0.72134752044448170f, x, r));",
+                  "relu = __builtin_amdgcn_fmed3f(x, 0.0f, gelu_reg(__builtin_inff()));",
+                  "return __builtin_fmaf(-gelu_mul0(x, u, r), e, relu);"]
+    statements += ["r = __builtin_fmaf(r, u, kGeluR%d);" % k for k in range(8)]
+    statements += ["r = __builtin_fmaf(r, u, kGeluS%d);" % k for k in range(4)]
+    assert [s for s in statements if s not in body] == []
+    assert body.count(";") == len(statements) + 1  # and the declaration of r
     assert 'asm("v_mul_legacy_f32 %0, |%1|, %2" : "=v"(v) : "v"(x), "v"(u), "v"(r));' in text
-    assert "return gelu_sum(x, gelu_mul0(x, u, r), gelu_exp(x, r));" in text
 
 
 def test_coefficients_match_fit_script():
