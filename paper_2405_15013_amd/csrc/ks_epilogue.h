@@ -67,13 +67,14 @@ constexpr float kGeluS5 = 10.5570784f;
 // batch-size-first the same (54 us, 51 since its operands are packed by
 // v_perm_b32: a tile of the DMA kernel runs these operations with none of its
 // own loads in flight and two workgroups per CU, so they add to the X stream
-// instead of running under it).  Of 500 batch-size-first DMA calls with bias and
-// GELU, batch 500 to 25088, the mean is 0.97 of the longer form's time; fifteen,
-// most with d = 16, are 1.03 to 1.14 times slower ((6,48,32,16) fp32 at batch 13020
-// 128 -> 145 us, (8,64,32,16) f16 at 14208 94 -> 99), although they issue fewer
+// instead of running under it).  Of 700 batch-size-first DMA calls with bias and
+// GELU, batch 500 to 25088, the mean is 0.97 of the longer form's time; 28, most
+// in fp32, are 1.03 to 1.17 times slower ((6,48,32,16) fp32 at batch 13020 128 ->
+// 138 us, (8,64,32,16) f16 at 14208 94 -> 99), although they issue fewer
 // operations.  Putting the next reciprocal and the last power of two under each
-// polynomial by hand gave 137 and 99 us there, 55 -> 52 us in the bf16 call above
-// and 97 -> 102 in the fp32 one: not kept.
+// polynomial by hand gave 137 and 99 us there, 0.99 of the time in 16 bits in the
+// mean and 97 -> 102 us in (6,64,16,8) fp32, other single calls 3 to 10 % slower:
+// not kept.
 // A constant in a vector register, for operands that take no literal.
 __device__ __forceinline__ float gelu_reg(float c) {
   asm("" : "+v"(c));
